@@ -188,6 +188,13 @@ template <typename T>
 hipError_t set_lds_limits_chain();
 template <typename T>
 size_t chain_lds_bytes(int ncb);
+// Items of both pipelines in one launch (FP32, complex64): workgroup b takes entries
+// 2 b and 2 b + 1 (an item of tiles of 64 in entry 2 b, or one or two items of tiles
+// of 32; nch = 0: none); 512 threads.  lds: the largest over the workgroups of
+// pipe_lds_bytes, or of the sum of chain_lds_bytes.  Phases as the two launches.
+hipError_t launch_mstage_mixed(const MItem* d_items, int nblocks, size_t lds, const void* src, void* dst, bool inverse,
+                               PhaseArgs ph, hipStream_t s);
+hipError_t set_lds_limits_mixed();
 
 // *flag = 1 if any value of the channels' data is a NaN or an infinity
 // (checked plans); the flag is cleared first by the same launcher.  One

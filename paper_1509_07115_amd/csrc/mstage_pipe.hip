@@ -34,7 +34,7 @@
 // Prefetch: the blocks of tile t + SETS are loaded into the registers that tile
 // t's matrix instructions have just read.  Every global read of a tile is at
 // least two steps before its write, so the stage runs in place.
-#include "kernels.h"
+#include "mstage_chain.h"
 
 #include <type_traits>
 
@@ -614,6 +614,35 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) m
     pipe_item<T, D, INV, KPH, KBMAX, 1>(it, src, dst, ph, lds_pipe);   // FP64 items have one column block
 }
 
+// Items of both tile sizes in one launch (FP32 plans with l on both sides of 64):
+// workgroup b takes entries 2 b and 2 b + 1 of the list, either an item of tiles of
+// 64 (entry 2 b, all eight waves) or two items of tiles of 32, four waves each, or
+// one and an empty entry.  Waves w and w + 4 share a SIMD, so the roles of the
+// second item are one place further along: each SIMD holds role r of one item and
+// r - 1 of the other (mstage_chain.h).  The two items meet at the same barriers; an
+// item with fewer tiles, or an empty entry, ends early, and the barrier then waits
+// for the waves that are left.  As two launches in turn each waits for its longest
+// chain: uneven batch of 512 channels (l <= 127, N to 8192), forward and inverse, 525
+// us as two launches, 390 in one; 3D step 64 x 17 x 4096 (l <= 71) 404 and 302.
+template <bool INV, bool KPH>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) mstage_mixed(const MItem* __restrict__ items, const void* src, void* dst,
+                                                    PhaseArgs ph) {
+    extern __shared__ __align__(16) unsigned char lds_pipe[];
+    const MItem* pair = items + 2 * blockIdx.x;
+    if (pair[0].B == 64) {
+        if (pair[0].NCB == 2) pipe_item<float, float, INV, KPH, 4, 2>(pair[0], src, dst, ph, lds_pipe);
+        else pipe_item<float, float, INV, KPH, 4, 1>(pair[0], src, dst, ph, lds_pipe);
+        return;
+    }
+    const int half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    const int role = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) + 3 * half) & 3;
+    const MItem& it = pair[half];
+    if (it.nch == 0) return;
+    float* lds = reinterpret_cast<float*>(lds_pipe) + (half ? chain::chain_lds_values(pair[0].NCB) : 0);
+    if (it.NCB == 2) chain::run_item<float, float, INV, KPH, 2>(it, src, dst, ph, lds, role);
+    else chain::run_item<float, float, INV, KPH, 1>(it, src, dst, ph, lds, role);
+}
+
 // One 16 x 16 block per workgroup (tile blockIdx.x, block blockIdx.y) of the
 // table of one direction from the FP64 blocks M_J[r][q] (row-major, R = 64 + k).
 // The weight w_0 of odd l is folded into slot 0 of tile 0.
@@ -695,6 +724,30 @@ hipError_t set_lds_limits_pipe() {
         set((const void*)mstage_pipe<T, double, false, false, 4>);
     }
     return e;
+}
+
+hipError_t launch_mstage_mixed(const MItem* d_items, int nblocks, size_t lds, const void* src, void* dst, bool inverse,
+                               PhaseArgs ph, hipStream_t s) {
+    if (nblocks <= 0) return hipSuccess;
+    if (!inverse && ph.use) return hipErrorInvalidValue;   // phases are applied to the inverse's input only
+    const dim3 grid(nblocks), block(512);
+    if (inverse && ph.use)
+        hipLaunchKernelGGL((mstage_mixed<true, true>), grid, block, lds, s, d_items, src, dst, ph);
+    else if (inverse)
+        hipLaunchKernelGGL((mstage_mixed<true, false>), grid, block, lds, s, d_items, src, dst, ph);
+    else
+        hipLaunchKernelGGL((mstage_mixed<false, false>), grid, block, lds, s, d_items, src, dst, ph);
+    return hipGetLastError();
+}
+
+hipError_t set_lds_limits_mixed() {
+    const int bytes = (int)(2 * chain_lds_bytes<float>(2));   // two items of two column blocks: the most of any entry pair
+    for (const void* f : {(const void*)mstage_mixed<true, false>, (const void*)mstage_mixed<true, true>,
+                          (const void*)mstage_mixed<false, false>}) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <typename T, typename D, int KBMAX>

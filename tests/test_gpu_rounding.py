@@ -44,3 +44,57 @@ def test_tiles_of_64_round_no_more_than_tiles_of_32(N):
         print(f"N={N} {call}: tiles of 32 {err[32]:.4g}, of 64 {err[64]:.4g}")
         assert err[64] <= err[32], (call, err)
 
+
+
+def _with_potential(chans, mode="batched"):
+    from paper_1509_07115_amd import Plan
+    plan = Plan(chans, mode=mode)
+    V = np.zeros(plan.elems)
+    for N, ell, rmax, off in chans:
+        V[off:off + N] = -1.0 / np.sqrt(((np.arange(N) + 0.5) * rmax / N) ** 2 + 0.01)
+    plan.set_potential(V, 0.02)
+    return plan
+
+
+# (sizes, l of the channels looked at, channels of each, l of the others, channels of each): more and
+# fewer items than compute units (two items of a tile size in a workgroup, or one), items of one and two
+# column blocks, one tile per channel, unequal sizes (items that share a workgroup end at different tiles)
+COMPANY = [((512,), (0, 1, 2, 15, 31, 32, 33, 62), 3, (71,), 1),
+           ((64, 512, 128), (0, 1, 2, 15, 31, 32, 33, 62), 2, (65, 96, 100), 3),
+           ((64,), tuple(range(0, 63, 3)), 9, (64, 70, 97, 126), 40),
+           ((32, 64, 256, 128), tuple(range(50)), 9, (64, 90, 110), 30),
+           ((64,), tuple(range(64)), 72, (100, 120), 100),
+           ((64,), (0, 5, 40), 9, tuple(range(64, 127)), 40)]
+
+
+@pytest.mark.parametrize("sizes,low,n_low,high,n_high", COMPANY)
+def test_fp32_results_do_not_depend_on_the_other_channels(sizes, low, n_low, high, n_high):
+    """complex64 channels with l <= 63 get the same bits with and without channels of
+    larger l in the plan: transforms, steps and adjoint steps; and the batched plan the
+    bits of the per-channel one."""
+    chans, off = [], 1
+    for N in sizes:
+        for ell, n in [(ell, n_low) for ell in low] + [(ell, n_high) for ell in high if N >= 64]:
+            if ell > 2 * N - 2:
+                continue
+            for _ in range(n):
+                chans.append((N, ell, 0.05 * N, off))
+                off += N + 1
+    alone = [c for c in chans if c[1] <= 63]
+    x = _random(off, torch.complex64, seed=7)
+    a, b, plain = _with_potential(alone), _with_potential(chans), _with_potential(chans, mode="plain")
+
+    def at(y, some):   # the values of some channels
+        return torch.cat([y[o:o + N] for N, _, _, o in some])
+
+    for call in ("forward", "inverse"):
+        got = getattr(b, call)(x)
+        assert torch.equal(at(getattr(a, call)(x), alone), at(got, alone)), call
+        assert torch.equal(at(getattr(plain, call)(x), chans), at(got, chans)), call
+    for adjoint in (False, True):
+        y, z, w = x.clone(), x.clone(), x.clone()
+        a.kinetic_step(y, 3, adjoint=adjoint)
+        b.kinetic_step(z, 3, adjoint=adjoint)
+        plain.kinetic_step(w, 3, adjoint=adjoint)
+        assert torch.equal(at(y, alone), at(z, alone)), adjoint
+        assert torch.equal(at(w, chans), at(z, chans)), adjoint
