@@ -1,13 +1,17 @@
 // Tile and batch-shape search for a channel set (dsbt_autotune).
 //
-// Candidates are the moment tile B (0 = the plan's own choice per l, 32, 64)
-// crossed with the channels per moment work item (0 = the plan's own choice,
+// Candidates are the moment tile B (0 = the plan's own choice per l, 32, and 64 for
+// FP64 arithmetic) crossed with the channels per moment work item (0 = the plan's own choice,
 // 8, 4).  Each candidate is a full plan; those the channel set does not admit
 // (a tile below ceil((l+1)/2) or above N) are skipped.  A candidate is timed
 // with HIP events over `nrep` forward + inverse pairs on device scratch
 // buffers, after one untimed pair.  The buffers hold hashed pseudo-random
 // values in [-1, 1): the transforms have no data-dependent control flow, but
 // constant data draws less power and can run at higher clocks than real data.
+//
+// Tiles of 64 are not tried for FP32 arithmetic: where they are faster than the
+// plan's own choice (l <= 63, few items) the norm grows more over many steps (the
+// tile rule of build_plan, capi.cpp), and a time cannot weigh that.
 //
 // Results are cached as JSON lines, one object per tuned channel set:
 //   {"key": "<16 hex>", "tile": B, "chans_per_block": C, "ms": t}
@@ -65,7 +69,7 @@ std::string cache_key(const dsbt_channel* ch, int nch, const dsbt_plan_opts& o) 
     return buf;
 }
 
-bool cache_lookup(const char* path, const std::string& key, int& tile, int& cpb, double& ms) {
+bool cache_lookup(const char* path, const std::string& key, int refused, int& tile, int& cpb, double& ms) {
     FILE* f = std::fopen(path, "r");
     if (!f) return false;
     char line[512];
@@ -79,7 +83,7 @@ bool cache_lookup(const char* path, const std::string& key, int& tile, int& cpb,
         const char* pc = std::strstr(line, "\"chans_per_block\":");
         const char* pm = std::strstr(line, "\"ms\":");
         if (pt && pc && pm && std::sscanf(pt + 7, "%d", &t) == 1 && std::sscanf(pc + 18, "%d", &c) == 1 &&
-            std::sscanf(pm + 5, "%lf", &m) == 1) {
+            std::sscanf(pm + 5, "%lf", &m) == 1 && t != refused) {
             tile = t;
             cpb = c;
             ms = m;
@@ -108,9 +112,10 @@ extern "C" dsbt_status dsbt_autotune(const dsbt_channel* ch, int32_t nch, const 
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || ndev <= 0) return DSBT_ERR_NO_DEVICE;
     const std::string key = cache_key(ch, nch, o);
+    const int refused = o.precision == DSBT_C64 ? 64 : -1;   // tile that is neither tried nor taken from the file
     int tile = 0, cpb = 0;
     double ms = 0;
-    if (cache_path && cache_lookup(cache_path, key, tile, cpb, ms)) {
+    if (cache_path && cache_lookup(cache_path, key, refused, tile, cpb, ms)) {
         *best = o;
         best->tile = tile;
         best->chans_per_block = cpb;
@@ -140,6 +145,7 @@ extern "C" dsbt_status dsbt_autotune(const dsbt_channel* ch, int32_t nch, const 
         result = DSBT_ERR_HIP;
     } else {
         for (int t : {0, 32, 64}) {
+            if (t == refused) continue;
             for (int c : {0, 8, 4}) {
                 dsbt_plan_opts cand = o;
                 cand.tile = t;

@@ -98,3 +98,28 @@ def test_fp32_results_do_not_depend_on_the_other_channels(sizes, low, n_low, hig
         plain.kinetic_step(w, 3, adjoint=adjoint)
         assert torch.equal(at(y, alone), at(z, alone)), adjoint
         assert torch.equal(at(w, chans), at(z, chans)), adjoint
+
+
+def test_autotuned_complex64_plans_keep_the_default_tile(tmp_path):
+    # few items, where tiles of 64 would be the fastest; then a stored line that holds one
+    import json
+
+    from paper_1509_07115_amd import Plan
+    chans = _packed(2048, [ell for ell in range(16) for _ in range(8)])
+    cache = tmp_path / "tune.jsonl"
+    first = Plan.autotuned(chans, nrep=5, cache=str(cache)).tuning
+    assert first["tile"] in (0, 32)
+    line = json.loads(cache.read_text())
+    line["tile"] = 64
+    cache.write_text(json.dumps(line) + "\n")
+    again = Plan.autotuned(chans, nrep=5, cache=str(cache))
+    assert again.tuning["tile"] in (0, 32) and len(cache.read_text().splitlines()) == 2
+    x = _random(2048 * len(chans), torch.complex64)
+    assert torch.equal(again.forward(x), Plan(chans).forward(x))
+    # FP64 arithmetic: a stored tile of 64 is taken
+    Plan.autotuned(chans, nrep=1, cache=str(cache), precision="c128")
+    lines = cache.read_text().splitlines()
+    line = json.loads(lines[-1])
+    line["tile"] = 64
+    cache.write_text("\n".join(lines[:-1] + [json.dumps(line)]) + "\n")
+    assert Plan.autotuned(chans, nrep=1, cache=str(cache), precision="c128").tuning["tile"] == 64
