@@ -99,7 +99,12 @@ typedef struct {
     int32_t mode;         /* DSBT_MODE_BATCHED (default) or DSBT_MODE_PLAIN */
     int32_t plan_where;   /* DSBT_PLAN_ON_DEVICE (default): the FP64 DLOP recurrences and tile
                              blocks are computed by GPU kernels; DSBT_PLAN_ON_HOST: by host threads */
-    int32_t tile;         /* moment tile B (power of two >= ceil((l+1)/2)); 0 = automatic */
+    int32_t tile;         /* moment tile B (power of two >= ceil((l+1)/2)); 0 = automatic.  The
+                             automatic tile of DSBT_C64 depends on l (and the smallest N with that
+                             l) only.  With FP64 arithmetic it also depends on how many channels
+                             the plan holds and on the device's compute units, so the same channel
+                             can round differently in a batch and in a part of it (its error stays
+                             the same); a tile set here gives the same rounding in both. */
     int32_t chans_per_block; /* channels per workgroup in the transform stage; 0 = automatic */
     int32_t algorithm;    /* DSBT_ALG_TILED (default) or DSBT_ALG_MONOMIAL, see below */
     int32_t check_finite; /* 0 (default) or 1: dsbt_forward, dsbt_inverse and dsbt_kinetic_step first

@@ -123,3 +123,19 @@ def test_autotuned_complex64_plans_keep_the_default_tile(tmp_path):
     line["tile"] = 64
     cache.write_text("\n".join(lines[:-1] + [json.dumps(line)]) + "\n")
     assert Plan.autotuned(chans, nrep=1, cache=str(cache), precision="c128").tuning["tile"] == 64
+
+
+@pytest.mark.parametrize("precision", ["c128", "c64x"])
+@pytest.mark.parametrize("N", [128, 512, 1024, 2048])
+def test_fp64_tile_follows_the_items_per_compute_unit(N, precision):
+    # one item of 8 channels per compute unit is the line, at every size; the bits of the
+    # results say which tile a plan took
+    from paper_1509_07115_amd import Plan
+    ncu = torch.cuda.get_device_properties(0).multi_processor_count
+    for items, tile in ((ncu // 2 + 16, 64), (ncu, 64), (ncu + 1, 32)):
+        ells = [3 + i % 13 for i in range(items)]          # 13 l, a remainder in some of them
+        chans = _packed(N, [ell for ell in sorted(ells) for _ in range(8)])
+        x = _random(N * len(chans), torch.complex64 if precision == "c64x" else torch.complex128)
+        b = Plan(chans, precision=precision).forward(x)
+        assert torch.equal(b, Plan(chans, precision=precision, tile=tile).forward(x)), (items, tile)
+        assert precision == "c64x" or not torch.equal(b, Plan(chans, precision=precision, tile=96 - tile).forward(x))
