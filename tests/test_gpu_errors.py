@@ -146,6 +146,48 @@ def test_plan_memory_through_the_caller_allocator():
     plan.close()
 
 
+@pytest.mark.parametrize("precision", ["c64", "c64x", "c128"])
+def test_later_potentials_allocate_and_free_nothing(precision):
+    # equal potentials share their tables, but a later call with more distinct ones must
+    # not need memory (dev_free is for dsbt_plan_destroy): a failing allocator changes nothing
+    chans = [(256, 2, 25.6, 0), (256, 2, 25.6, 256), (128, 5, 12.8, 512), (256, 70, 25.6, 640)]
+    live, calls, closed = {}, [], [False]
+
+    def held_bytes():
+        from paper_1509_07115_amd import _lib
+        n = ctypes.c_int64()
+        assert _lib.load().dsbt_plan_info(plan._h, None, None, None, ctypes.byref(n)) == 0
+        return n.value
+
+    def alloc(n):
+        calls.append("alloc")
+        if closed[0]:
+            return 0
+        t = torch.empty(int(n), dtype=torch.uint8, device="cuda")
+        live[t.data_ptr()] = t
+        return t.data_ptr()
+
+    def free(ptr):
+        calls.append("free")
+        del live[ptr]
+
+    plan = Plan(chans, precision=precision, allocator=(alloc, free))
+    plan.set_potential(np.zeros(plan.elems), 0.01)
+    held, before = held_bytes(), set(live)
+    del calls[:]
+    closed[0] = True
+    x = torch.randn(plan.elems, dtype=plan.dtype, device="cuda")
+    rng = np.random.default_rng(2)
+    for V in (rng.standard_normal(plan.elems), np.ones(plan.elems), rng.standard_normal(plan.elems)):
+        plan.set_potential(V, 0.01)
+        other = Plan(chans, precision=precision)
+        other.set_potential(V, 0.01)
+        assert torch.equal(plan.kinetic_step(x.clone(), 2), other.kinetic_step(x.clone(), 2))
+    assert not calls and held_bytes() == held and set(live) == before
+    plan.close()
+    assert not live
+
+
 def test_angular_diagonal_tables_from_the_library():
     # K = k_n^2/2 per coefficient slot (eq. KinMat) and -2 k~_n eta_j on the
     # momentum grid, built behind the C ABI, against their definitions
