@@ -507,7 +507,10 @@ __global__ void __launch_bounds__(256) axis_mfma64(const double* __restrict__ ma
 // tasks by eta_j, and Legendre tasks by (m, parity of t) forward, by (m, block of
 // eta_j) inverse; the first step reads memory, the second writes it.
 // Element pairs are always added: the table entries of a self-paired element
-// (k = 0, the middle node) carry the factor 1/2.  Contraction indices past the end
+// (k = 0, the middle node) carry the factor 1/2.  The sum of two finite values must
+// not overflow where the result does not, so values are halved before it by powers of
+// two that cancel: forward the loads by 1/4, the DFT tables carry 2 and the Legendre
+// tables 2; inverse the Legendre tables carry 1/2 and the DFT tables 2.  Contraction indices past the end
 // are clamped and meet zero table entries; result rows past the end are copies of
 // the last row and are written onto it (LDS) or masked (memory).
 // 64 x 17 x 4096 (256 workgroups): forward 19.3 us, inverse 22.7 (two launches:
@@ -585,13 +588,16 @@ __global__ void __launch_bounds__(64 * kShtWaves) sht_both(const float* __restri
         for (int b = 0; b < MB; ++b)
 #pragma unroll
             for (int v = 0; v < 4 && 4 * b + v < KS; ++v) {
-                const float2 p = x[b][v], n = y[b][v];
+                const float h = INV ? 1.f : 0.25f;   // (the products by h are exact)
+                const float2 p = float2{h * x[b][v].x, h * x[b][v].y}, n = y[b][v];
+                const float er = fmaf(h, n.x, p.x), ei = fmaf(h, n.y, p.y);
+                const float dr = fmaf(-h, n.x, p.x), di = fmaf(-h, n.y, p.y);
 #pragma unroll
                 for (int a = 0; a < MB; ++a) {
-                    E[a][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(C[a][b][v], p.x + n.x, E[a][0], 0, 0, 0);
-                    E[a][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(C[a][b][v], p.y + n.y, E[a][1], 0, 0, 0);
-                    O[a][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(S[a][b][v], p.x - n.x, O[a][0], 0, 0, 0);
-                    O[a][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(S[a][b][v], p.y - n.y, O[a][1], 0, 0, 0);
+                    E[a][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(C[a][b][v], er, E[a][0], 0, 0, 0);
+                    E[a][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(C[a][b][v], ei, E[a][1], 0, 0, 0);
+                    O[a][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(S[a][b][v], dr, O[a][0], 0, 0, 0);
+                    O[a][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(S[a][b][v], di, O[a][1], 0, 0, 0);
                 }
             }
         unsigned char* lb = lds_sht + j * nphi * lrow;
@@ -973,8 +979,8 @@ static void sht_blocks(const std::vector<double>& P, int nt, int nphi, bool inve
                             const bool middle = 2 * j == nt - 1;
                             if (t >= nt || j >= H || (e && middle)) continue;
                             const double* p = P.data() + ((size_t)q * nt + t) * nt;
-                            // equal up to rounding and the sign (-1)^t
-                            o[4 * l + v] = 0.5 * (p[j] + (e ? -p[nt - 1 - j] : p[nt - 1 - j]));
+                            // equal up to rounding and the sign (-1)^t; times 2 (forward) or 1/2
+                            o[4 * l + v] = (inverse ? 0.25 : 1.0) * (p[j] + (e ? -p[nt - 1 - j] : p[nt - 1 - j]));
                             if (middle && !inverse) o[4 * l + v] *= 0.5;   // its sum is z + z
                         }
                 }
@@ -987,7 +993,7 @@ void sht_both_tables(const std::vector<double>& P, int nt, int nphi, std::vector
     sht_blocks(P, nt, nphi, true, inv);
     leg.insert(leg.end(), inv.begin(), inv.end());
     const int M = (nphi - 1) / 2, MB = M / 16 + 1;
-    const double pi = 3.14159265358979323846, sc = 1.0 / std::sqrt((double)nphi);
+    const double pi = 3.14159265358979323846, sc = 2.0 / std::sqrt((double)nphi);
     dft.assign((size_t)2 * MB * MB * 256, 0.0);
     for (int a = 0; a < MB; ++a)
         for (int b = 0; b < MB; ++b)

@@ -149,3 +149,35 @@ def test_both_steps_in_one_launch(nt, nphi, nr):
             call(room[:n], out=out)
             got = out.cpu().numpy()
             assert np.linalg.norm(got - want) <= 2e-6 * np.linalg.norm(want), (call.__name__, off)
+
+
+@pytest.mark.parametrize("nt,nphi,nr", [(64, 17, 20), (33, 11, 16), (64, 1, 40), (9, 1, 3), (20, 63, 530)])
+def test_one_launch_takes_values_up_to_the_largest(nt, nphi, nr):
+    """A power of two times the data is the same power of two times the result (to one
+    rounding, and to terms below the normal range of the unscaled result), up to the
+    largest finite values: the symmetric and antisymmetric sums of element and node pairs
+    must not overflow where the result does not.  Two values of nearly 2^128 per point:
+    an azimuth pair (+k, -k), a node pair (j, -j), equal and opposite."""
+    from paper_1509_07115_amd import AngularTransform
+    Y = AngularTransform(nr, nt, nphi)
+    rng = np.random.default_rng(nt + nphi)
+    grid, coef = np.zeros((nt, nphi, nr), np.complex64), np.zeros((nphi, nt, nr), np.complex64)
+    for i in range(nr):
+        j, k, q, t = (int(rng.integers(n)) for n in (nt, nphi, nphi, nt))
+        v = np.complex64(complex(*rng.uniform(1.7, 1.99, 2)))
+        s = (1, -1)[i // 2 % 2]
+        grid[j, k, i] = v
+        grid[(j, (nphi - k) % nphi, i) if i % 2 else (nt - 1 - j, k, i)] += s * v * (i % 2 == 0 or k > 0)
+        grid[j, k, i] = v
+        coef[q, t, i] = v
+        coef[nphi - 1 - q, t, i] = s * v
+    two = 2.0 ** 127
+    for call, x in ((Y.forward, grid), (Y.inverse, coef)):
+        small = torch.from_numpy(x.reshape(-1)).cuda()
+        large = torch.view_as_complex(torch.view_as_real(small) * two)
+        assert torch.isfinite(torch.view_as_real(large)).all()
+        want = torch.view_as_real(call(small)) * two
+        got = torch.view_as_real(call(large))
+        ok = torch.isfinite(want)                    # (a result of 2 or more overflows in earnest)
+        assert ok.float().mean() > 0.9
+        assert torch.allclose(got[ok], want[ok], rtol=2.0 ** -23, atol=two * 2.0 ** -120), call.__name__
