@@ -107,3 +107,48 @@ def test_sine_cosine_stage_of_every_size(sizes, precision):
                 chans.append((N, ell, 0.1 * N, off))
                 off += N + 1
     _check(chans, off, precision)
+
+
+def _check_steps(chans, total, precision, kind, sample):
+    """Two steps against the dense oracle on the sampled channels: two transforms and their
+    phase products per step, errors relative to the input (no factor is above one)."""
+    from paper_1509_07115_amd import Plan
+    dt = 0.02
+    rng = np.random.default_rng(total)
+    x = rng.standard_normal(total) + 1j * rng.standard_normal(total)
+    V = np.abs(rng.standard_normal(total))
+    plan = Plan(chans, precision=precision)
+    plan.set_potential(V, dt, imaginary=kind == "imaginary")
+    xd = torch.from_numpy(x).to(_dtype(precision)).cuda()
+    got = plan.kinetic_step(xd.clone(), 2, adjoint=kind == "adjoint").cpu().numpy()
+    x0 = xd.cpu().numpy().astype(np.complex128)
+    tol = 2 * (2 * TOL[precision] + 4e-7 * (precision == "c64"))
+    for N, ell, rmax, off in sample:
+        s = slice(off, off + N)
+        E, ref = otdse.kinetic_energies(N, rmax, ell), x0[s]
+        for _ in range(2):
+            ref = (otdse.imag_step(ref, ell, V[s], E, dt) if kind == "imaginary" else
+                   otdse.step(ref, ell, V[s], E, dt, adjoint=kind == "adjoint"))
+        assert np.linalg.norm(got[s] - ref) <= tol * np.linalg.norm(x0[s]), (kind, N, ell, off)
+
+
+@pytest.mark.parametrize("precision", ["c64", "c64x", "c128"])
+@pytest.mark.parametrize("kind", ["step", "adjoint", "imaginary"])
+def test_steps_with_two_to_four_moment_blocks(kind, precision):
+    # the kinetic factors at the edges of the moment blocks, one to four tiles, beside channels
+    # of small l, with remainders of channels
+    chans, off = [], 1
+    for N in (64, 128, 256):
+        for ell, n in ((3, 2), (33, 9), (64, 1), (65, 9), (95, 1), (96, 3), (97, 8), (126, 9), (127, 1)):
+            for _ in range(n if ell <= 2 * N - 2 else 0):
+                chans.append((N, ell, 0.1 * N, off))
+                off += N + 3
+    _check_steps(chans, off, precision, kind, chans)
+
+
+@pytest.mark.parametrize("kind", ["step", "adjoint", "imaginary"])
+def test_steps_of_two_column_blocks(kind):
+    # FP32 with more items of 8 channels than compute units: items of 16 channels, whose column
+    # blocks share the kinetic factors; 41 channels per l leave an item of 8 and one of 1
+    chans, total = _channels(64, [(ell, 41) for ell in range(64, 127)], gap=1)
+    _check_steps(chans, total, "c64", kind, [c for i, c in enumerate(chans) if i % 41 in (0, 8, 15, 31, 32, 40)])

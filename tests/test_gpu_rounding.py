@@ -139,3 +139,30 @@ def test_fp64_tile_follows_the_items_per_compute_unit(N, precision):
         b = Plan(chans, precision=precision).forward(x)
         assert torch.equal(b, Plan(chans, precision=precision, tile=tile).forward(x)), (items, tile)
         assert precision == "c64x" or not torch.equal(b, Plan(chans, precision=precision, tile=96 - tile).forward(x))
+
+
+def test_forty_fp32_steps_of_small_and_large_l_in_one_plan():
+    """complex64 against complex128 after 40 steps of random data, 112 channels with l <= 62
+    and 96 with l >= 64.  Per step the error is that of two transforms and three unit
+    factors, 40 steps add it up at random: sqrt(40) (1.41e-7^2 + 1.57e-7^2 + 3 (1.1e-7)^2)^.5
+    = 1.8e-6 for l <= 62 (the transforms' measured errors), with a fifth more allowed for
+    what is not random; sums over up to 128 slots and moments may add another tenth.  The
+    norm may grow by 3e-7 (2.0e-7 before there were tiles of 64 in FP32 plans)."""
+    from paper_1509_07115_amd import Plan
+    N = 2048
+    high = [ell for ell in (64, 65, 70, 80, 90, 95, 96, 97, 100, 110, 120, 127) for _ in range(8)]
+    chans = _packed(N, LOW + high)
+    x = _random(N * len(chans), torch.complex64)
+    V = np.tile(-1.0 / np.sqrt(((np.arange(N) + 0.5) * 0.05) ** 2 + 0.01), len(chans))
+    y = {}
+    for precision in ("c64", "c128"):
+        plan = Plan(chans, precision=precision)
+        plan.set_potential(V, 0.01)
+        y[precision] = plan.kinetic_step(x.to(plan.dtype, copy=True), 40).to(torch.complex128).reshape(-1, N)
+    cut = len(LOW)
+    for name, s, bound in (("l <= 62", slice(0, cut), 2.2e-6), ("l >= 64", slice(cut, None), 2.4e-6)):
+        a, b = y["c64"][s], y["c128"][s]
+        err = (torch.linalg.vector_norm(a - b) / torch.linalg.vector_norm(b)).item()
+        growth = (torch.linalg.vector_norm(a) / torch.linalg.vector_norm(b)).item() - 1.0
+        print(f"{name}: error {err:.3e}, norm {growth:+.3e}")
+        assert err <= bound and abs(growth) <= 3e-7, name
