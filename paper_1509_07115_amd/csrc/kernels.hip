@@ -1,8 +1,8 @@
 // HIP kernels of the orthogonal DSBT for CDNA4 (gfx950): the generic moment
-// stage (complex128 plans and items the matrix-core kernel does not take) and
-// the reduction of the strength gradient.  The sine/cosine stage lives in
-// fstage.hip, the matrix-core moment stage in mstage_pipe.hip and
-// mstage_chain.hip.
+// stage (tiles other than 32 and 64: N = 16, l above 127, or a tile that the
+// caller sets) and the reduction of the strength gradient.  The sine/cosine
+// stage lives in fstage.hip, the matrix-core moment stage of every precision in
+// mstage_chain.h (tiles of 32) and mstage_pipe.hip (tiles of 64).
 //
 // Stage M (Sec. 2.4-2.5): the Fourier-to-Bessel matrix T applied as a sequence
 // of tile steps [b_J; mu_J+1] = M_J [g_J; mu_J] (forward) or

@@ -41,7 +41,7 @@
 // B[l/16][l%16]; result register v of lane l is D[4 (l/16) + v][l%16]
 // (v_mfma_f64_16x16x4_f64: the same operands, result row 4 v + l/16).  The 16
 // columns of block cb are channels 8 cb .. 8 cb + 7 times (re, im).  Operands
-// use the table layout of MItem::mf_f / mf_i with NB = 4 (per tile, row block
+// use the table layout of MItem::mf_f / mf_i (per tile, row block
 // rb and group g of 4 chunks, 64 lanes x the 4 values A'[16 rb + l%16][4 kc +
 // l/16]).  Zero blocks are skipped: the in-tile band of T and the
 // moment-to-moment block are triangular (lower forward, upper inverse), and

@@ -54,7 +54,7 @@ template <> struct Vec<double> {
     static __device__ v4 mfma(double a, double b, v4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 };
 
-constexpr int kXRing = 4;   // tile data: written in step t, read until step t + kSkew
+constexpr int kXRing = 4;   // tile data: written in step t, last read in step t + 2 (a power of two of slots)
 constexpr int kRing = 2;    // q and moments: written in one step, read in the next
 
 // The blocks of one tile.  Row block rb of the tile slots takes blocks
