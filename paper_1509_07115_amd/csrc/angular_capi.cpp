@@ -43,13 +43,24 @@ hipError_t upload(const std::vector<double>& h, void** d) {
 }
 
 // One launch or two for a complex64 transform.  A workgroup of the one-launch
-// kernel takes 16 points through both steps, 7 to 13 us however few there are; the
-// two launches split further (16 points x eta, then 64 points x m).  Forward and
-// inverse, us, one / two launches: 64 x 17 values of 4096 points 40 / 90, 1024
-// points 28 / 39, 512 points 26.5 / 26.0, 16 points 25.3 / 21.6; 64 x 15 values of
+// kernel takes 16 points through both steps, 7 to 13 us however few there are, two
+// workgroups to a compute unit; the two launches split further (16 points x eta, then
+// 64 points x m), and pack small angular grids better.
+// Few points, forward and inverse, us on one / two launches (the kernels alone, on
+// data in the caches): 64 x 17 values of 4096 points 40 / 90, 1024 points 28 / 39,
+// 512 points 26.5 / 26.0, 16 points 25.3 / 21.6; 64 x 15 values of
 // 512 points 23.3 / 23.1, 16 x 45 of 512 22.2 / 21.5; up to 64 x 11 one launch is
 // faster at every size (704 values, 16 points: 19.1 / 21.1).
-bool one_launch(int nt, int nphi, int Nr) { return Nr > 512 || nt * nphi <= 704; }
+// Many points, forward / inverse on one against two launches (calls back to back, so
+// not below 9 and 12): up to 8192 points one launch is ahead for every grid; 16384:
+// 4 x 1 8 9 / 12 12, 32 x 1 13 11 / 12 12, 64 x 1 22 22 / 20 20, 8 x 7 11 11 / 12 12,
+// 32 x 7 18 18 / 24 24; 32768: 8 x 1 12 10 / 12 12, 32 x 1 24 19 / 18 18, 16 x 7 25 22 /
+// 21 21, 8 x 15 28 22 / 28 27, 32 x 7 31 32 / 41 40; 131072: 1 x 1 31 25 / 13 13, 64 x 1
+// 158 223 / 104 103, 8 x 7 72 55 / 46 46, 8 x 15 96 77 / 102 106, 4 x 31 143 148 / 137 146.
+bool one_launch(int nt, int nphi, int Nr) {
+    if (Nr > 16384 && (nphi < 7 || nt * nphi < 120)) return false;
+    return Nr > 512 || nt * nphi <= 704;
+}
 
 template <typename S>
 hipError_t run(dsbt_sht_s* p, const void* src, void* dst, bool inverse, hipStream_t s) {

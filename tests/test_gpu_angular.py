@@ -181,3 +181,47 @@ def test_one_launch_takes_values_up_to_the_largest(nt, nphi, nr):
         ok = torch.isfinite(want)                    # (a result of 2 or more overflows in earnest)
         assert ok.float().mean() > 0.9
         assert torch.allclose(got[ok], want[ok], rtol=2.0 ** -23, atol=two * 2.0 ** -120), call.__name__
+
+
+def _us_per_call(f, n=20):
+    best = float("inf")
+    for _ in range(5):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(n):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / n)
+    return best
+
+
+@pytest.mark.parametrize("nt,nphi,nr", [(1, 1, 1 << 19), (4, 1, 1 << 18)])
+def test_many_points_of_a_small_angular_grid_are_not_held_up(nt, nphi, nr):
+    """A transform reads and writes its data once or twice: four copies' time and the two
+    launches are ample (one workgroup per 16 points takes twice that)."""
+    from paper_1509_07115_amd import AngularTransform
+    Y = AngularTransform(nr, nt, nphi)
+    x = torch.randn(Y.size, 2, device="cuda").view(-1, 2)
+    x = torch.view_as_complex(x)
+    out = torch.empty_like(x)
+    copy = _us_per_call(lambda: out.copy_(x))
+    for call in (Y.forward, Y.inverse):
+        t = _us_per_call(lambda: call(x, out=out))
+        print(f"{nt} x {nphi} x {nr} {call.__name__}: {t:.1f} us, copy {copy:.1f}")
+        assert t <= 4 * copy + 12
+
+
+# both sides of the line between one launch and two for many points
+@pytest.mark.parametrize("nt,nphi,nr", [(3, 1, 16384), (3, 1, 16385), (17, 7, 16401), (18, 7, 16401), (24, 5, 16390),
+                                        (8, 15, 16400), (40, 1, 20001)])
+def test_many_points(nt, nphi, nr):
+    from paper_1509_07115_amd import AngularTransform
+    rng = np.random.default_rng(nr + nt)
+    psi = rng.standard_normal((nt, nphi, nr)) + 1j * rng.standard_normal((nt, nphi, nr))
+    Y = AngularTransform(nr, nt, nphi)
+    for call, ref in ((Y.forward, angular.forward(psi, nt, nphi)),
+                      (Y.inverse, angular.inverse(psi.reshape(nphi, nt, nr), nt, nphi))):
+        want = np.asarray(ref).reshape(-1)
+        got = call(dev(psi, Y.dtype)).cpu().numpy()
+        assert np.linalg.norm(got - want) <= 2e-6 * np.linalg.norm(want), call.__name__
