@@ -17,12 +17,17 @@
 //   four result waves   one row block of o = W x + E mu each, stored to memory
 //
 // Lane layouts (lane l, quarter q = l/16, column l%16).  Every block of 16 rows
-// of a vector is held as four values per lane, rows 4 q .. 4 q + 3.  That is the
-// result layout of v_mfma_f32_16x16x4_f32 (row 4 q + v in register v), and of
-// v_mfma_f64_16x16x4_f64 (row 4 v + q) with the table's rows permuted; and as
+// of a vector is held as four values per lane: of the tile's slots rows 4 q .. 4 q
+// + 3 (contiguous in memory), of the moments rows q, 4 + q, 8 + q, 12 + q.  One is
+// the result layout of v_mfma_f32_16x16x4_f32 (row 4 q + v in register v), the other
+// that of v_mfma_f64_16x16x4_f64 (row 4 v + q); the table's rows are permuted for
+// the one that an instruction does not have; and as
 // the contraction index may be permuted alike in both operands (instruction v
-// takes rows 4 q + v), it is the operand layout too: results need no
-// rearrangement on the serial path.  The tables hold for each tile its non-zero
+// takes register v of every lane), they are the operand layouts too: results need no
+// rearrangement on the serial path.  (Moments: instruction v then takes the
+// consecutive rows 4 v .. 4 v + 3, so that in the triangular D nothing but zeros is
+// added after the diagonal term, or, in the inverse with the instructions from the
+// last, little; each later term would round at the moment's size, in every tile.)  The tables hold for each tile its non-zero
 // 16 x 16 blocks (the in-tile band and D are triangular), 4 values per lane, in
 // the order of the roles: 19, 29, 40 or 52 blocks for KB = 1 .. 4.
 //
@@ -68,10 +73,13 @@ __host__ __device__ constexpr int d_hi(bool inv, int kb, int rb) { return inv ? 
 // Column block (0..3 data, 4.. moments) of the i-th block of result row block rb, in
 // the order of its products: data farthest from the diagonal first, then the moments,
 // the diagonal block last.  The diagonal terms are the largest; added first, every
-// later sum rounds at their size.  FP32, N = 2048, l <= 62, error against 64 bits,
-// diagonal block first (inverse) or before the moments (forward) / last: forward
-// 1.42e-7 / 1.31e-7, inverse 1.68e-7 / 1.37e-7 (tiles of 32: 1.41e-7, 1.57e-7); l = 64 to
-// 127: 1.85e-7 / 1.60e-7 and 2.09e-7 / 1.74e-7.  The order costs nothing.
+// later sum rounds at their size; and the sums over the data and over the moments are
+// kept apart until the end.  The order costs nothing.  FP32 errors against 64 bits,
+// diagonal first (inverse) or before the moments (forward), one sum / now (with the
+// order of D's terms above): random data of N = 2048, l <= 62, forward 1.42e-7 / 1.31e-7,
+// inverse 1.68e-7 / 1.36e-7 (tiles of 32: 1.41e-7, 1.57e-7); l = 64 to 127 1.85e-7 /
+// 1.52e-7 and 2.09e-7 / 1.58e-7; Gaussian sums of N = 8192, l = 96 to 127, 2.82e-7 /
+// 2.54e-7 and 3.44e-7 / 2.63e-7.
 __host__ __device__ constexpr int out_col(bool inv, int kb, int rb, int i) {
     const int n = x_hi(inv, rb) - x_lo(inv, rb) - 1;
     return i < n ? (inv ? 3 - i : i) : i < n + kb ? 4 + i - n : rb;
@@ -87,6 +95,8 @@ __host__ __device__ constexpr int b_d(bool inv, int kb, int rb) {
     for (int r = 0; r < rb; ++r) b += d_hi(inv, kb, r) - d_lo(inv, r);
     return b;
 }
+// column block of the i-th block of moment row block rb: the diagonal block last
+__host__ __device__ constexpr int d_col(bool inv, int kb, int i) { return inv ? kb - 1 - i : i; }
 __host__ __device__ constexpr int b_all(bool inv, int kb) { return b_d(inv, kb, kb); }
 __host__ __device__ constexpr int moment_blocks(int k) { return k > 16 ? (k + 15) / 16 : 1; }
 
@@ -223,12 +233,16 @@ struct Pipe64 {
     __device__ unsigned char* q_at(int t, int cb, int b) const { return qring + (t % kRing) * MSLOT + (cb * KB + b) * BLK; }
 
     // c[cb] += a x[cb]: one 16 x 16 block, four instructions; two accumulators
-    // per column block when only one is in flight
+    // per column block when only one is in flight.  REV: the instructions from the last
+    template <bool REV = false>
     static __device__ void mma(V4 (*c)[2], V4 a, const V4* x) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) c[cb][v & 1] = Vec<T>::mfma(a[v], x[cb][v], c[cb][v & 1]);
+            for (int cb = 0; cb < NCB; ++cb) {
+                const int v = REV ? 3 - u : u;
+                c[cb][v & 1] = Vec<T>::mfma(a[v], x[cb][v], c[cb][v & 1]);
+            }
     }
     static __device__ V4 zero4() { return V4{0, 0, 0, 0}; }
 
@@ -433,9 +447,9 @@ struct Pipe64 {
         use_blocks<ND>(r.a[S], t, b_d(INV, KB, 0), [&](int i) {
 #pragma unroll
             for (int h = 0; h < KB; ++h) {   // block i of D: row block h, column block b
-                const int b = i - (b_d(INV, KB, h) - b_d(INV, KB, 0)) + d_lo(INV, h);
-                if (i >= b_d(INV, KB, h) - b_d(INV, KB, 0) && i < b_d(INV, KB, h + 1) - b_d(INV, KB, 0))
-                    mma(c[h], r.a[S][i], r.mu[b]);
+                const int n = i - (b_d(INV, KB, h) - b_d(INV, KB, 0));
+                if (n >= 0 && i < b_d(INV, KB, h + 1) - b_d(INV, KB, 0))
+                    mma<INV>(c[h], r.a[S][i], r.mu[d_col(INV, KB, n)]);
             }
         });
         if constexpr (kSkew == 3) chain_q(r, t + 1);   // (past the last tile: an old value, not used)
@@ -460,7 +474,7 @@ struct Pipe64 {
                 for (int v = 0; v < 4; ++v) {
                     T x = 0;
                     if constexpr (INV) {
-                        const int row = 16 * h + 4 * q + v;
+                        const int row = 16 * h + 4 * v + q;
                         const int n = row < k ? row : 0;
                         T re = (T)src[e0[cb] + 2 * n], im = (T)src[e0[cb] + 2 * n + 1];
                         if constexpr (KPH) {
@@ -492,7 +506,7 @@ struct Pipe64 {
                 for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const int row = 16 * h + 4 * q + v;
+                        const int row = 16 * h + 4 * v + q;
                         if (row < k) dst[e0[cb] + 2 * row + odd] = (D)(sgn * r.mu[h][cb][v]);
                     }
         }
@@ -515,17 +529,17 @@ struct Pipe64 {
     template <int RB, int S>
     __device__ void out_step(Out<RB>& r, int t) const {
         if constexpr (kSkew == 2) out_x(r, t);
-        V4 m[KB][NCB], c[NCB][2];
+        V4 m[KB][NCB], c[NCB][2], e[NCB][2];
 #pragma unroll
         for (int h = 0; h < KB; ++h)
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb) m[h][cb] = ld_lds(m_at(t, cb, h));
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) c[cb][0] = c[cb][1] = zero4();
+        for (int cb = 0; cb < NCB; ++cb) c[cb][0] = c[cb][1] = e[cb][0] = e[cb][1] = zero4();
         use_blocks<Out<RB>::N>(r.a[S], t, b_out(INV, KB, RB), [&](int i) {
             const int col = out_col(INV, KB, RB, i);
             if (col < 4) mma(c, r.a[S][i], r.x[col < 4 ? col - x_lo(INV, RB) : 0]);
-            else mma(c, r.a[S][i], m[col < 4 ? 0 : col - 4]);
+            else mma(e, r.a[S][i], m[col < 4 ? 0 : col - 4]);
         });
         if constexpr (kSkew == 3) out_x(r, t + 1);   // staged two steps ago (past the last tile: an old slot, not used)
         // a lane holds rows 4 q + v of the re (even) or im (odd) part: the pair
@@ -535,7 +549,7 @@ struct Pipe64 {
         const int n0 = 64 * tile(t) + 16 * RB + 4 * q + 2 * odd;
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
-            const V4 o = c[cb][0] + c[cb][1];
+            const V4 o = (c[cb][0] + c[cb][1]) + (e[cb][0] + e[cb][1]);
             const D w[4] = {(D)o[0], (D)o[1], (D)o[2], (D)o[3]};
             const D s0 = swap_pair(w[0]), s1 = swap_pair(w[1]), s2 = swap_pair(w[2]), s3 = swap_pair(w[3]);
             *reinterpret_cast<D4 DSBT_GLOBAL*>(dst + e0[cb] + 2 * (int64_t)n0) =
@@ -664,15 +678,17 @@ __global__ void __launch_bounds__(64) pack_blocks(const double* __restrict__ blo
     } else {
         while (u >= b_d(inv, kb, rb + 1)) ++rb;
         row0 = 64 + 16 * rb;
-        col0 = 64 + 16 * (d_lo(inv, rb) + u - b_d(inv, kb, rb));
+        col0 = 64 + 16 * d_col(inv, kb, u - b_d(inv, kb, rb));
     }
     const int i = lane & 15, q = lane >> 4;
-    // FP64 results come back as row 4 v + q in register v: permute the rows
-    const int row = row0 + (sizeof(T) == sizeof(double) ? 4 * (i & 3) + (i >> 2) : i);
+    // result row i of the instruction is at lane quarter i / 4, register i % 4 (FP64 the
+    // other way round): permuted where that is not the lane layout of the rows
+    const bool swap = (row0 >= 64) != (sizeof(T) == sizeof(double));
+    const int row = row0 + (swap ? 4 * (i & 3) + (i >> 2) : i);
     const double* M = blocks + (size_t)J * R * R;
     T* o = out + ((size_t)J * gridDim.y + u) * 256;
     for (int v = 0; v < 4; ++v) {
-        const int col = col0 + 4 * q + v;
+        const int col = col0 + (col0 >= 64 ? 4 * v + q : 4 * q + v);
         double a = 0.0;
         if (row < R && col < R) {
             a = inv ? M[(size_t)col * R + row] : M[(size_t)row * R + col];

@@ -46,6 +46,27 @@ def test_tiles_of_64_round_no_more_than_tiles_of_32(N):
 
 
 
+def test_long_chains_of_large_l():
+    """Errors over 128 tiles, against complex128: the channels of the uneven batch with N =
+    8192 and l >= 96.  Bounds 5% above what an FP32 sum over each block row in column order
+    gives (2.53e-7 forward), and a tenth below the inverse's 3.44e-7, whose terms came in
+    the worst order."""
+    from paper_1509_07115_amd import Plan, workloads
+    w = workloads.uneven()
+    chans = [c for c in w.channels if c[0] == 8192 and c[1] >= 96]
+    assert len(chans) > 10
+    x = torch.from_numpy(w.psi).to(torch.complex64).cuda()
+    plan, exact = Plan(chans), Plan(chans, precision="c128")
+    b = plan.forward(x)
+    for name, got, ref, bound in (("forward", b, exact.forward(x.to(torch.complex128)), 2.66e-7),
+                                  ("inverse", plan.inverse(b), exact.inverse(b.to(torch.complex128)), 3.1e-7)):
+        errs = [(torch.linalg.vector_norm(got[o:o + N] - ref[o:o + N]) / torch.linalg.vector_norm(ref[o:o + N])).item()
+                for N, _, _, o in chans]
+        rms = float(np.sqrt(np.mean(np.square(errs))))
+        print(f"{name}: rms {rms:.3e}, largest {max(errs):.3e}")
+        assert rms <= bound, name
+
+
 def _with_potential(chans, mode="batched"):
     from paper_1509_07115_amd import Plan
     plan = Plan(chans, mode=mode)
