@@ -188,6 +188,12 @@ template <typename T>
 hipError_t set_lds_limits_chain();
 template <typename T>
 size_t chain_lds_bytes(int ncb);
+// The operand table of one direction (MItem::mf_f / mf_i of B = 32 items, NT 64 x 64
+// values), packed on the device from the FP64 blocks M_J[r][q] of NT tiles (R = 32 + k).
+template <typename T>
+size_t chain_table_bytes(int NT) { return (size_t)NT * 4096 * sizeof(T); }
+template <typename T>
+hipError_t launch_pack_chain(const double* d_blocks, int k, int p, int NT, bool inverse, void* out, hipStream_t s);
 // Items of both pipelines in one launch (FP32, complex64): workgroup b takes entries
 // 2 b and 2 b + 1 (an item of tiles of 64 in entry 2 b, or one or two items of tiles
 // of 32; nch = 0: none); 512 threads.  lds: the largest over the workgroups of

@@ -29,7 +29,36 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof
     run_item<T, D, INV, KPH, 1>(it, src, dst, ph, lds, wave);   // FP64 items have one column block
 }
 
+// The operand table of one direction (kernels.h) from the FP64 blocks M_J[r][q] (row-major,
+// R = 32 + k): workgroup (J, rb), thread = (group g, lane l).  The weight w_0 of odd l is
+// folded into slot 0 of tile 0.
+template <typename T>
+__global__ void __launch_bounds__(256) pack_chain(const double* __restrict__ blocks, int k, int p, int inverse,
+                                                  T* __restrict__ out) {
+    const int J = blockIdx.x, rb = blockIdx.y, g = threadIdx.x >> 6, l = threadIdx.x & 63, R = 32 + k;
+    const int row = 16 * rb + (l & 15);
+    const double* M = blocks + (size_t)J * R * R;
+    T* o = out + ((size_t)J * 4 + rb) * 1024 + 256 * g + 4 * l;
+    for (int c = 0; c < 4; ++c) {
+        const int col = 4 * (4 * g + c) + (l >> 4);
+        double a = 0.0;
+        if (row < R && col < R) {
+            a = inverse ? M[(size_t)col * R + row] : M[(size_t)row * R + col];
+            if (J == 0 && p == 0 && (inverse ? row : col) == 0) a *= 0.70710678118654752440;
+        }
+        o[c] = (T)a;
+    }
+}
+
 }  // namespace
+
+template <typename T>
+hipError_t launch_pack_chain(const double* d_blocks, int k, int p, int NT, bool inverse, void* out, hipStream_t s) {
+    if (k < 0 || k > 32 || NT < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(pack_chain<T>, dim3(NT, 4), dim3(256), 0, s, d_blocks, k, p, inverse ? 1 : 0,
+                       static_cast<T*>(out));
+    return hipGetLastError();
+}
 
 template <typename T>
 size_t chain_lds_bytes(int ncb) {
@@ -71,6 +100,8 @@ hipError_t launch_mstage_chain(const MItem* d_items, int nitems, int ncb, const 
     return hipGetLastError();
 }
 
+template hipError_t launch_pack_chain<float>(const double*, int, int, int, bool, void*, hipStream_t);
+template hipError_t launch_pack_chain<double>(const double*, int, int, int, bool, void*, hipStream_t);
 template size_t chain_lds_bytes<float>(int);
 template size_t chain_lds_bytes<double>(int);
 template hipError_t set_lds_limits_chain<float>();

@@ -198,32 +198,6 @@ void build_ftb_blocks(int ell, int B, int NT, std::vector<double>& blocks, int n
     for (auto& th : pool) th.join();
 }
 
-void arrange_mfma_blocks(const std::vector<double>& blocks, int k, int p, int NT, bool inverse,
-                         std::vector<double>& out) {
-    const int R = 32 + k;
-    if (R > 64) throw std::invalid_argument("arrange_mfma_blocks: block larger than the padded size");
-    out.assign((size_t)NT * 64 * 64, 0.0);
-    const double w0 = std::sqrt(0.5);
-    for (int J = 0; J < NT; ++J) {
-        const double* M = blocks.data() + (size_t)J * R * R;
-        for (int rb = 0; rb < 4; ++rb) {
-            for (int l = 0; l < 64; ++l) {
-                const int row = 16 * rb + (l % 16);
-                // group g = kc / 4 of lane l: 64 lanes x 4 values contiguous
-                double* o = out.data() + ((size_t)J * 4 + rb) * 1024 + 4 * l;
-                for (int kc = 0; kc < 16; ++kc) {
-                    const int q = 4 * kc + l / 16;
-                    if (row >= R || q >= R) continue;
-                    double v = inverse ? M[(size_t)q * R + row] : M[(size_t)row * R + q];
-                    // slot 0 of tile 0 is m = 0 for odd l, weighted by w_0
-                    if (J == 0 && p == 0 && (inverse ? row == 0 : q == 0)) v *= w0;
-                    o[(kc / 4) * 256 + kc % 4] = v;
-                }
-            }
-        }
-    }
-}
-
 // j_l(x) and j_{l+1}(x), x > 0, FP64: upward recurrence from j_0, j_1 where it
 // is stable (x well above l), else Miller's downward recurrence normalised by
 // j_0 (or j_1 near a zero of j_0).

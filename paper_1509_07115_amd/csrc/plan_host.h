@@ -41,13 +41,6 @@ int auto_tile(int ell, int N);
 // `nthreads` host threads are used (0 = hardware concurrency).
 void build_ftb_blocks(int ell, int B, int NT, std::vector<double>& blocks, int nthreads);
 
-// Rearrange row-major blocks of tiles of 32 into the matrix-core operand layout (see
-// MItem::mf_f in kernels.h): A' = M_J (forward) or M_J^T (inverse), padded to
-// 64 x 64 (k <= 32), with the weight w_0 = 1/sqrt(2) of odd l folded into the slot-0
-// column (forward) or row (inverse) of tile 0.
-void arrange_mfma_blocks(const std::vector<double>& blocks, int k, int p, int NT, bool inverse,
-                         std::vector<double>& out);
-
 // Momenta k of the kinetic diagonal in slot order (N values): the completion
 // rows take N dk; regular row n takes x_j / rmax with x_j the j-th positive
 // root (j = n - n0 + 1) of chi_l(x) = x j_l(x) for even l or of chi_l'(x) for
