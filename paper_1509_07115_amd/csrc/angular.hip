@@ -515,7 +515,7 @@ __global__ void __launch_bounds__(256) axis_mfma64(const double* __restrict__ ma
 // the last row and are written onto it (LDS) or masked (memory).
 // 64 x 17 x 4096 (256 workgroups): forward 19.3 us, inverse 22.7 (two launches:
 // 48 each); the 71 MB alone take 14 at the rate of a large copy.  A workgroup by
-// itself takes 9 to 10 us, of which 4.3 are matrix instructions, so the loads of a
+// itself takes 9 to 10 us, of which 6.2 are matrix instructions, so the loads of a
 // wave's next tasks are issued together and addresses are lane offset + wave offset
 // of a buffer (with 64-bit lane addresses a workgroup took 15 us).
 constexpr int kShtPts = 16, kShtWaves = 16;
