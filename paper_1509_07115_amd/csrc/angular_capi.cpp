@@ -51,15 +51,23 @@ hipError_t upload(const std::vector<double>& h, void** d) {
 // 512 points 26.5 / 26.0, 16 points 25.3 / 21.6; 64 x 15 values of
 // 512 points 23.3 / 23.1, 16 x 45 of 512 22.2 / 21.5; up to 64 x 11 one launch is
 // faster at every size (704 values, 16 points: 19.1 / 21.1).
-// Many points, forward / inverse on one against two launches (calls back to back, so
-// not below 9 and 12): up to 8192 points one launch is ahead for every grid; 16384:
-// 4 x 1 8 9 / 12 12, 32 x 1 13 11 / 12 12, 64 x 1 22 22 / 20 20, 8 x 7 11 11 / 12 12,
-// 32 x 7 18 18 / 24 24; 32768: 8 x 1 12 10 / 12 12, 32 x 1 24 19 / 18 18, 16 x 7 25 22 /
-// 21 21, 8 x 15 28 22 / 28 27, 32 x 7 31 32 / 41 40; 131072: 1 x 1 31 25 / 13 13, 64 x 1
-// 158 223 / 104 103, 8 x 7 72 55 / 46 46, 8 x 15 96 77 / 102 106, 4 x 31 143 148 / 137 146.
+// Many points, forward and inverse on one / two launches (calls back to back, so not
+// below 8 and 11).  Where a point holds few values, or one or three per node, the two
+// launches' packing wins from 20480 points on (five workgroups to a compute unit); of
+// the smallest grids both are short launches up to 32768; five values per node follow
+// beyond 65536 points where the nodes fill more than two tiles of 16:
+// 20480 points: 4 x 1 8 8 / 11 11, 16 x 1 11 9 / 11 11, 64 x 1 25 26 / 24 24, 16 x 5
+// 14 12 / 16 17, 64 x 3 31 39 / 34 34; 24576: 32 x 1 17 14 / 14 14, 48 x 1 26 26 / 24 24,
+// 16 x 7 18 16 / 17 17; 32768: 8 x 1 11 9 / 11 11, 64 x 1 39 39 / 32 32, 48 x 3 41 51 /
+// 36 35, 16 x 5 22 18 / 17 17; 98304: 1 x 1 24 19 / 11 11, 64 x 1 120 172 / 78 78, 64 x 3
+// 165 243 / 150 161, 40 x 5 149 198 / 144 148, 64 x 5 205 276 / 242 240.  The other
+// side: 8 x 15 32768 27 22 / 26 26, 98304 73 58 / 68 74; 32 x 5 32768 29 26 / 30 30, 98304 82 71 / 90 96; 64 x 5 20480 36 42 / 53 53, 65536
+// 139 186 / 160 158; 64 x 7 98304 233 326 / 329 328; 48 x 9 98304 213 374 / 298 298.
 bool one_launch(int nt, int nphi, int Nr) {
-    if (Nr > 16384 && (nphi < 7 || nt * nphi < 120)) return false;
-    return Nr > 512 || nt * nphi <= 704;
+    const int values = nt * nphi;
+    const int few = nt > 32 && Nr > 65536 ? 7 : 5;
+    if (Nr > (values < 16 ? 32768 : 20480) && (values < 120 || nphi < few)) return false;
+    return Nr > 512 || values <= 704;
 }
 
 template <typename S>

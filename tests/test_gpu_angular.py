@@ -214,7 +214,10 @@ def test_many_points_of_a_small_angular_grid_are_not_held_up(nt, nphi, nr):
 
 # both sides of the line between one launch and two for many points
 @pytest.mark.parametrize("nt,nphi,nr", [(3, 1, 16384), (3, 1, 16385), (17, 7, 16401), (18, 7, 16401), (24, 5, 16390),
-                                        (8, 15, 16400), (40, 1, 20001)])
+                                        (8, 15, 16400), (40, 1, 20001),
+                                        (16, 1, 20480), (16, 1, 20481), (23, 5, 20483), (24, 5, 20483), (40, 3, 20481),
+                                        (15, 1, 32768), (15, 1, 32769), (5, 3, 32771),
+                                        (33, 5, 65536), (33, 5, 65537)])
 def test_many_points(nt, nphi, nr):
     from paper_1509_07115_amd import AngularTransform
     rng = np.random.default_rng(nr + nt)
