@@ -61,8 +61,9 @@ hipError_t upload(const std::vector<double>& h, void** d) {
 // 16 x 7 18 16 / 17 17; 32768: 8 x 1 11 9 / 11 11, 64 x 1 39 39 / 32 32, 48 x 3 41 51 /
 // 36 35, 16 x 5 22 18 / 17 17; 98304: 1 x 1 24 19 / 11 11, 64 x 1 120 172 / 78 78, 64 x 3
 // 165 243 / 150 161, 40 x 5 149 198 / 144 148, 64 x 5 205 276 / 242 240.  The other
-// side: 8 x 15 32768 27 22 / 26 26, 98304 73 58 / 68 74; 32 x 5 32768 29 26 / 30 30, 98304 82 71 / 90 96; 64 x 5 20480 36 42 / 53 53, 65536
-// 139 186 / 160 158; 64 x 7 98304 233 326 / 329 328; 48 x 9 98304 213 374 / 298 298.
+// side: 8 x 15 32768 27 22 / 26 26, 98304 73 58 / 68 74; 32 x 5 32768 29 26 / 30 30,
+// 98304 82 71 / 90 96; 64 x 5 20480 36 42 / 53 53, 65536 139 186 / 160 158; 64 x 7 98304
+// 233 326 / 329 328; 48 x 9 98304 213 374 / 298 298.
 bool one_launch(int nt, int nphi, int Nr) {
     const int values = nt * nphi;
     const int few = nt > 32 && Nr > 65536 ? 7 : 5;
